@@ -259,7 +259,7 @@ int64_t encode_scratch(int64_t n) {
 
 // Encodes with the caller's scratch (encode_scratch(n) bytes), or, without any,
 // with one allocated for the call (one block: ten allocations and releases took a
-// quarter of an encode); synchronises.
+// quarter of an encode); synchronises, whether it succeeds or not.
 gp_status encode_volume(const float* means, const float* attrs, int64_t n, int64_t stride, uint16_t* codes_out,
                         int64_t stride_out, uint32_t* perm_out, float* d_hdr, void* scratch, hipStream_t s) {
   void* own = nullptr;
@@ -272,7 +272,9 @@ gp_status encode_volume(const float* means, const float* attrs, int64_t n, int64
   size_t bytes = 0;
   const CodecScratch t = codec_scratch(scratch ? scratch : own, n, &bytes);
   hipError_t e = launch_encode(means, attrs, n, stride, codes_out, stride_out, perm_out, d_hdr, t, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  // (also after an error: what was launched before it still writes the scratch)
+  const hipError_t waited = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = waited;
   const gp_status st = e == hipSuccess ? GP_OK : hip_fail(e, "encode");
   if (own) (void)hipFree(own);
   return st;
