@@ -279,8 +279,9 @@ typedef struct gp_codec_header {
 gp_status gp_encode(const float* d_params, int64_t n, int64_t stride, uint16_t* d_codes, int64_t stride_out,
                     uint32_t* d_perm, float* d_header, void* stream);
 
-/* gp_encode with the caller's scratch: at least gp_encode_scratch(n) bytes of
- * device memory aligned to 256 (0 for an n that gp_encode refuses), free for other
+/* gp_encode with the caller's scratch: at least gp_encode_scratch(n) bytes (about
+ * 37 n; gp_encode allocates as much for the call) of device memory aligned to 256
+ * (0 for an n that gp_encode refuses), free for other
  * use once the call returns, also with an error.  Allocates nothing; synchronises
  * on stream. */
 int64_t gp_encode_scratch(int64_t n);

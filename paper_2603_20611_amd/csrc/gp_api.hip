@@ -433,8 +433,8 @@ gp_status enqueue_forward(Workspace* ws, RenderConst rc, const LaunchDims& d, hi
     bool ranged = false;
     const uint32_t* d_end = ws->d_ctr + kCtrSortEnd;   // before the first overflowed Gaussian's slots
     hipError_t e = launch_radix_sort(ws->d_inst_key, ws->d_inst_val, ws->d_key2, ws->d_val2, d_count, d_end,
-                                     std::max<int64_t>(n_sort, 1), bits, ws->d_hist,
-                                     reinterpret_cast<uint32_t*>(ws->d_scan_part), s, &ws->d_list_key, &ws->d_list,
+                                     std::max<int64_t>(n_sort, 1), bits, ws->d_hist, s,
+                                     &ws->d_list_key, &ws->d_list,
                                      ws->d_bin_lo, ws->d_bin_hi, ws->bin_cap, &ranged);
     if (e == hipSuccess && !ranged)
       e = launch_bin_ranges(ws->d_hdr, ws->d_list_key, d_count, d_end, icap, ws->d_bin_lo, ws->d_bin_hi, s);
@@ -831,8 +831,8 @@ gp_status gp_voxelize(gp_workspace* w, const gp_gaussians* g, const gp_volume_gr
     ws->last_stream = s;
     GP_HIP(launch_vox_emit(*ws, g, grid, o, L, s));
     GP_HIP(launch_radix_sort(ws->d_inst_key, ws->d_inst_val, ws->d_key2, ws->d_val2, ws->d_ctr + kCtrInstances, nullptr,
-                             std::max<int64_t>(K, 1), bits, ws->d_hist, reinterpret_cast<uint32_t*>(ws->d_scan_part),
-                             s, &ws->d_list_key, &ws->d_list));
+                             std::max<int64_t>(K, 1), bits, ws->d_hist, s, &ws->d_list_key,
+                             &ws->d_list));
     GP_HIP(launch_vox_ranges(*ws, L, (uint32_t)K, s));
     GP_HIP(launch_vox_fwd(*ws, g, grid, o, L, vol, s));
   }

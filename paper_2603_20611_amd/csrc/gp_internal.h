@@ -341,7 +341,7 @@ int radix_passes(int bits);
 int64_t radix_hist_entries(int bits, int64_t cap);
 hipError_t launch_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* d_count,
                              const uint32_t* d_count2,
-                             int64_t cap, int bits, uint32_t* hist, uint32_t* scan_part, hipStream_t s,
+                             int64_t cap, int bits, uint32_t* hist, hipStream_t s,
                              uint32_t** k_out, uint32_t** v_out, uint32_t* lo = nullptr, uint32_t* hi = nullptr,
                              int64_t n_ranges = 0, bool* ranges = nullptr);
 hipError_t launch_bin_ranges(const BatchHdr* hdr, const uint32_t* key, const uint32_t* d_count,
@@ -363,10 +363,9 @@ hipError_t launch_preprocess_bwd(const RenderConst& rc, const Workspace& ws, flo
 struct CodecScratch {
   uint32_t* bounds;     // nine per workgroup of the bounds kernel
   uint32_t* count;      // [1]
-  uint4* codes;         // [n][2]: eleven 16-bit codes each, in the original order
+  uint4* codes;         // [n]: the eight 12-bit codes and the Morton key's low part, in the original order
   uint32_t *key_lo, *key_hi, *idx, *key2, *val2;   // [n] each
   uint32_t* hist;       // radix_hist_entries of both stages' bits
-  uint32_t* scan_part;  // scan_parts_needed of the histogram
 };
 hipError_t launch_encode(const float* means, const float* attrs, int64_t n, int64_t stride, uint16_t* codes_out,
                          int64_t stride_out, uint32_t* perm_out, float* d_hdr, const CodecScratch& t, hipStream_t s);

@@ -16,7 +16,12 @@
 // that order: five passes) -> the codes gathered in Morton order.  Bound by the
 // sort's launches.  Minima and maxima by atomics on nine shared words took 0.049
 // ms for 500,000 Gaussians (now 0.012 and 0.004), gathers of 2-byte codes from 11 planes
-// 0.060 (one 32-byte record per Gaussian: 0.012), a split at 32 bits six passes.
+// 0.060 (one record per Gaussian: 0.012), a split at 32 bits six passes.
+//
+// A record is 16 bytes: the eight 12-bit codes and the low part of the Morton key, from
+// which, with the sorted high part, the three position codes are read back.  With the
+// sort's five arrays that is 36 bytes of scratch per Gaussian (52 with the codes spelled
+// out in 32 bytes, which made the largest set that can be encoded smaller).
 #include "gp_internal.h"
 
 #include <algorithm>
@@ -134,6 +139,16 @@ __device__ __forceinline__ uint64_t spread3_64(uint32_t v) {
   return x;
 }
 
+// The inverse of spread3_64: bits 0, 3, 6, ... of x.
+__device__ __forceinline__ uint32_t gather3_64(uint64_t x) {
+  x &= 0x249249249249ull;
+  x = (x | (x >> 2)) & 0x0C30C30C30C3ull;
+  x = (x | (x >> 4)) & 0x00F00F00F00Full;
+  x = (x | (x >> 8)) & 0x0000FF0000FFull;
+  x = (x | (x >> 16)) & 0x3FFFull;
+  return (uint32_t)x;
+}
+
 __global__ __launch_bounds__(256) void k_codec_codes(const float* __restrict__ m, const float* __restrict__ at,
                                                      int64_t n, int64_t stride,
                                                      const float* __restrict__ hdr, uint4* __restrict__ codes,
@@ -163,10 +178,11 @@ __global__ __launch_bounds__(256) void k_codec_codes(const float* __restrict__ m
     c[6 + r] = isfinite(cc) ? (uint32_t)fminf(fmaxf(cc, 0.0f), kAttrLevels1) : 0u;
   }
   c[10] = code_of(fmaxf(prow(m, at, stride, 10, j), 0.0f), 0.0f, hdr[8], kAttrLevels1);
-  codes[2 * j] = make_uint4(c[0] | (c[1] << 16), c[2] | (c[3] << 16), c[4] | (c[5] << 16), c[6] | (c[7] << 16));
-  codes[2 * j + 1] = make_uint4(c[8] | (c[9] << 16), c[10], 0u, 0u);
   const uint64_t key = spread3_64(c[0]) | (spread3_64(c[1]) << 1) | (spread3_64(c[2]) << 2);
-  key_lo[j] = (uint32_t)key & ((1u << kLowBits) - 1u);
+  const uint32_t lo = (uint32_t)key & ((1u << kLowBits) - 1u);
+  codes[j] = make_uint4(c[3] | (c[4] << 12) | (c[5] << 24), (c[5] >> 8) | (c[6] << 4) | (c[7] << 16) | (c[8] << 28),
+                        (c[8] >> 4) | (c[9] << 8) | (c[10] << 20), lo);
+  key_lo[j] = lo;
   key_hi[j] = (uint32_t)(key >> kLowBits);
   idx[j] = (uint32_t)j;
 }
@@ -178,17 +194,23 @@ __global__ __launch_bounds__(256) void k_codec_gather_u32(const uint32_t* __rest
   if (i < n) dst[i] = src[perm[i]];
 }
 
+// key_hi: the sorted high parts of the keys (in the order of perm).
 __global__ __launch_bounds__(256) void k_codec_gather_codes(const uint4* __restrict__ src,
-                                                            const uint32_t* __restrict__ perm, int64_t n,
+                                                            const uint32_t* __restrict__ perm,
+                                                            const uint32_t* __restrict__ key_hi, int64_t n,
                                                             int64_t stride_out, uint16_t* __restrict__ dst,
                                                             uint32_t* __restrict__ perm_out) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const uint32_t j = perm[i];
-  const uint4 a = src[2 * (size_t)j], b = src[2 * (size_t)j + 1];
-  const uint32_t w[6] = {a.x, a.y, a.z, a.w, b.x, b.y};
+  const uint4 v = src[j];
+  const uint64_t key = ((uint64_t)key_hi[i] << kLowBits) | v.w;
+  const uint32_t c[11] = {gather3_64(key), gather3_64(key >> 1), gather3_64(key >> 2),
+                          v.x & 0xFFFu, (v.x >> 12) & 0xFFFu, (v.x >> 24) | ((v.y & 0xFu) << 8),
+                          (v.y >> 4) & 0xFFFu, (v.y >> 16) & 0xFFFu, (v.y >> 28) | ((v.z & 0xFFu) << 4),
+                          (v.z >> 8) & 0xFFFu, v.z >> 20};
 #pragma unroll
-  for (int r = 0; r < 11; ++r) dst[r * stride_out + i] = (uint16_t)(w[r >> 1] >> (16 * (r & 1)));
+  for (int r = 0; r < 11; ++r) dst[r * stride_out + i] = (uint16_t)c[r];
   if (perm_out) perm_out[i] = j;
 }
 
@@ -205,7 +227,7 @@ hipError_t launch_encode(const float* means, const float* attrs, int64_t n, int6
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // stable sort by the low key bits, then by the high ones (keys gathered in that order)
   uint32_t *k_sorted = nullptr, *i_sorted = nullptr;
-  e = launch_radix_sort(t.key_lo, t.idx, t.key2, t.val2, t.count, nullptr, n, kLowBits, t.hist, t.scan_part, s, &k_sorted, &i_sorted);
+  e = launch_radix_sort(t.key_lo, t.idx, t.key2, t.val2, t.count, nullptr, n, kLowBits, t.hist, s, &k_sorted, &i_sorted);
   if (e != hipSuccess) return e;
   uint32_t* hi_perm = (k_sorted == t.key_lo) ? t.key2 : t.key_lo;   // the buffer the sort left free
   k_codec_gather_u32<<<blocks, 256, 0, s>>>(t.key_hi, i_sorted, n, hi_perm);
@@ -213,9 +235,9 @@ hipError_t launch_encode(const float* means, const float* attrs, int64_t n, int6
   uint32_t* i_free = (i_sorted == t.idx) ? t.val2 : t.idx;
   uint32_t* v_alt = (hi_perm == t.key_lo) ? t.key2 : t.key_lo;
   uint32_t *k2 = nullptr, *perm = nullptr;
-  e = launch_radix_sort(hi_perm, i_sorted, v_alt, i_free, t.count, nullptr, n, kHighBits, t.hist, t.scan_part, s, &k2, &perm);
+  e = launch_radix_sort(hi_perm, i_sorted, v_alt, i_free, t.count, nullptr, n, kHighBits, t.hist, s, &k2, &perm);
   if (e != hipSuccess) return e;
-  k_codec_gather_codes<<<blocks, 256, 0, s>>>(t.codes, perm, n, stride_out, codes_out, perm_out);
+  k_codec_gather_codes<<<blocks, 256, 0, s>>>(t.codes, perm, k2, n, stride_out, codes_out, perm_out);
   return hipGetLastError();
 }
 
@@ -237,7 +259,7 @@ static CodecScratch codec_scratch(void* block, int64_t n, size_t* bytes) {
   };
   auto u32 = [&](int64_t count) { return reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (size_t)count)); };
   CodecScratch t{};
-  t.codes = reinterpret_cast<uint4*>(take(32 * (size_t)nn));
+  t.codes = reinterpret_cast<uint4*>(take(sizeof(uint4) * (size_t)nn));
   t.bounds = u32(9 * kBoundsBlocks);
   t.count = u32(1);
   t.key_lo = u32(nn);
@@ -246,7 +268,6 @@ static CodecScratch codec_scratch(void* block, int64_t n, size_t* bytes) {
   t.key2 = u32(nn);
   t.val2 = u32(nn);
   t.hist = u32(hist);
-  t.scan_part = u32(2 * scan_parts_needed(hist));
   *bytes = at;
   return t;
 }

@@ -713,7 +713,7 @@ static void launch_scatter(int pb, unsigned grid, const RadixArgs& a, hipStream_
 // buffers that hold the result.  With `ranges` given, the last pass may also form
 // the bin ranges lo / hi (all ones and 0 before): *ranges tells.
 hipError_t launch_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* d_count,
-                             const uint32_t* d_count2, int64_t cap, int bits, uint32_t* hist, uint32_t* scan_part, hipStream_t s,
+                             const uint32_t* d_count2, int64_t cap, int bits, uint32_t* hist, hipStream_t s,
                              uint32_t** k_out, uint32_t** v_out, uint32_t* lo, uint32_t* hi, int64_t n_ranges,
                              bool* ranges) {
   if (ranges) *ranges = false;
