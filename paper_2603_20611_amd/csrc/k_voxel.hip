@@ -114,7 +114,7 @@ constexpr float kVoxSmooth = -4.0f;
 template <int DT>
 __global__ __launch_bounds__(256) void k_vox_count(VoxArgs a) {
   // the forward's reset of the tile ranges
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < a.n_tiles; i += gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n_tiles; i += (int64_t)gridDim.x * 256) {
     a.tile_lo[i] = 0u;
     a.tile_hi[i] = 0u;
   }
@@ -585,7 +585,10 @@ hipError_t launch_vox_count(const Workspace& ws, const gp_gaussians* g, const gp
                             const gp_render_opts* o, const VoxLaunch& L, hipStream_t s) {
   if (L.n <= 0) return hipSuccess;
   const VoxArgs a = vox_args(ws, g, grid, o, L);
-  const unsigned blocks = (unsigned)((L.n + 255) / 256);
+  // enough workgroups for the reset of the tile ranges too (16 tiles per thread): 64
+  // Gaussians on a million tiles 0.465 -> 0.320 ms (65,536 there 0.351)
+  const int64_t reset_blocks = std::min<int64_t>((L.n_tiles + 4095) / 4096, 16384);
+  const unsigned blocks = (unsigned)std::max<int64_t>(((int64_t)L.n + 255) / 256, reset_blocks);
   switch (g->attr_dtype) {
     case GP_BF16: k_vox_count<GP_BF16><<<blocks, 256, 0, s>>>(a); break;
     case GP_F16: k_vox_count<GP_F16><<<blocks, 256, 0, s>>>(a); break;
