@@ -287,9 +287,13 @@ __device__ __forceinline__ void backward_one(const BwdPreArgs& a, int n_groups, 
 // with them more lanes per Gaussian: 2,000 Gaussians on 32 slices had run on
 // four workgroups, one lane per chain of a dozen records (0.096 -> 0.012 ms),
 // 50,003 on 24 slices on 98 (0.127 -> 0.029 ms; 1,024 or 2,048 workgroups the
-// same, but 2 to 7 % slower for the whole 8-slice iteration on 500,000).
+// same, but 2 to 7 % slower for the whole 8-slice iteration on 500,000).  Batches of
+// one or two slices have short chains and few Gaussians per chunk with any: they take
+// kBwdGroupsFew (262,000 Gaussians on one slice 16.9 us with 512 workgroups, 15.1 with
+// 128, 100,000 on two 14.4 and 12.6, 5,000 on two 10.9 either way and 15.2 with chunks
+// of 512; on four slices 131,000 take 15.6 and 16.7).
 constexpr int kBwdChunk = 512;
-constexpr int kBwdGroups = 512;
+constexpr int kBwdGroups = 512, kBwdGroupsFew = 128;
 
 // The workgroup's list of n Gaussians, L lanes each, in rounds of 256 / L
 // (the bound is uniform over the workgroup, so every lane of a group reaches
@@ -367,7 +371,8 @@ hipError_t launch_preprocess_bwd(const RenderConst& rc, const Workspace& ws, flo
                ws.st_n,
                ws.d_poses,
                kBwdChunk};
-  while (a.chunk > 32 && d.gauss < (int64_t)kBwdGroups * a.chunk) a.chunk /= 2;
+  const int64_t groups = d.emit_width <= 2 ? kBwdGroupsFew : kBwdGroups;
+  while (a.chunk > 32 && d.gauss < groups * a.chunk) a.chunk /= 2;
   int64_t blocks = (d.gauss + a.chunk - 1) / a.chunk;
   if (blocks > 16384) blocks = 16384;
   return d.posed ? launch_bwd_p<true>(a, rc.attr_dtype, (unsigned)blocks, s)
