@@ -435,7 +435,8 @@ gp_status enqueue_forward(Workspace* ws, RenderConst rc, const LaunchDims& d, hi
     hipError_t e = launch_radix_sort(ws->d_inst_key, ws->d_inst_val, ws->d_key2, ws->d_val2, d_count, d_end,
                                      std::max<int64_t>(n_sort, 1), bits, ws->d_hist, s,
                                      &ws->d_list_key, &ws->d_list,
-                                     ws->d_bin_lo, ws->d_bin_hi, ws->bin_cap, &ranged);
+                                     ws->d_bin_lo, ws->d_bin_hi, ws->bin_cap,
+                                     d.sort_bins == 0 || d.sort_bins >= d.bins, &ranged);
     if (e == hipSuccess && !ranged)
       e = launch_bin_ranges(ws->d_hdr, ws->d_list_key, d_count, d_end, icap, ws->d_bin_lo, ws->d_bin_hi, s);
     return e;

@@ -343,7 +343,7 @@ hipError_t launch_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t*
                              const uint32_t* d_count2,
                              int64_t cap, int bits, uint32_t* hist, hipStream_t s,
                              uint32_t** k_out, uint32_t** v_out, uint32_t* lo = nullptr, uint32_t* hi = nullptr,
-                             int64_t n_ranges = 0, bool* ranges = nullptr);
+                             int64_t n_ranges = 0, bool whole = false, bool* ranges = nullptr);
 hipError_t launch_bin_ranges(const BatchHdr* hdr, const uint32_t* key, const uint32_t* d_count,
                              const uint32_t* d_count2, int64_t cap,
                              uint32_t* lo, uint32_t* hi, hipStream_t s);

@@ -12,8 +12,9 @@
 //            rank among equal digits: within a wavefront by matching digits
 //            bit by bit with ballots, across the block's eight wavefronts
 //            through per-digit counts in LDS.
-// A small sort has no scan kernel (its scatters add up their rows themselves) and
-// its last pass also forms the bins' ranges.
+// A sort of at most 2^21 pairs also forms the bins' ranges in its last pass, and a pass
+// of at most 6 bits over at most 512 tiles has no scan kernel (its scatter adds up
+// the rows itself).
 // Element counts are read from the device, so launches sized for a capacity
 // serve any batch (graph replay).
 #include "gp_internal.h"
@@ -236,6 +237,7 @@ struct RadixArgs {
   uint32_t* lo;           // bin ranges, formed by the last pass of a small sort (else null)
   uint32_t* hi;
   uint32_t n_ranges;      // their length
+  uint32_t by_total;      // the digit is the whole key: the ranges follow from the digits' totals
   uint32_t cap;           // element capacity
   int nblocks, shift, bits;
 };
@@ -514,6 +516,12 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(RadixArgs a) {
     for (int h = 0; h < kDigPerThread; ++h) {
       const int i = kDigPerThread * threadIdx.x + h;
       gofs[h] = g[h] + pr - p;
+      if constexpr (PW == kPerWaveSmall) {
+        if (a.lo && a.by_total && tile == 0u && rt[h] != 0u && (uint32_t)i < a.n_ranges) {
+          a.lo[i] = pr;
+          a.hi[i] = pr + rt[h];
+        }
+      }
       pr += rt[h];
       if (i < R) {
         uint32_t q = p;
@@ -559,7 +567,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(RadixArgs a) {
       a.val_out[dst] = sv[p];
       if constexpr (PW == kPerWaveSmall) {
         // a bin's pairs of this tile are neighbours here and in the output
-        if (a.lo && k < a.n_ranges) {
+        if (a.lo && !a.by_total && k < a.n_ranges) {
           if (p == 0 || sk[p - 1] != k) atomicMin(&a.lo[k], dst);
           if (p + 1 == tn || sk[p + 1] != k) atomicMax(&a.hi[k], dst + 1u);
         }
@@ -711,11 +719,14 @@ static void launch_scatter(int pb, unsigned grid, const RadixArgs& a, hipStream_
 // low `bits` bits of the key.
 // Ping-pongs between (k0, v0) and (k1, v1); returns in *k_out / *v_out the
 // buffers that hold the result.  With `ranges` given, the last pass may also form
-// the bin ranges lo / hi (all ones and 0 before): *ranges tells.
+// the bin ranges lo / hi (all ones and 0 before): *ranges tells.  A sort of one pass
+// does so from its digits' totals, and only if the keys have no higher bits (`whole`):
+// with atomics from every tile on a few dozen bins the sort of 1.4 million pairs on 64
+// bins took 126 us, so 19 (24 with a launch for the ranges).
 hipError_t launch_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, const uint32_t* d_count,
                              const uint32_t* d_count2, int64_t cap, int bits, uint32_t* hist, hipStream_t s,
                              uint32_t** k_out, uint32_t** v_out, uint32_t* lo, uint32_t* hi, int64_t n_ranges,
-                             bool* ranges) {
+                             bool whole, bool* ranges) {
   if (ranges) *ranges = false;
   const int passes = radix_passes(bits);
   *k_out = k0;
@@ -730,16 +741,17 @@ hipError_t launch_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t*
     const int shift = p * db;
     const int pb = std::min(db, bits - shift);
     uint32_t* rowtot = hist + ((size_t)1 << db) * nblocks;
-    RadixArgs a{ki, vi, ko, vo, hist, rowtot, d_count, d_count2, nullptr, nullptr, 0u, (uint32_t)cap, nblocks, shift, pb};
+    RadixArgs a{ki, vi, ko, vo, hist, rowtot, d_count, d_count2, nullptr, nullptr, 0u, 0u, (uint32_t)cap, nblocks, shift, pb};
     const unsigned grid = 8u * (unsigned)((nblocks + 7) / 8);
     if (small) {
       // (a launch costs about as much as a pass over a few hundred thousand
       // pairs: the small sorts' last pass forms the bin ranges, and their
       // scatters scan the counts where the rows are few and short)
-      if (ranges && p + 1 == passes) {
+      if (ranges && p + 1 == passes && (whole || passes > 1)) {
         a.lo = lo;
         a.hi = hi;
         a.n_ranges = (uint32_t)n_ranges;
+        a.by_total = passes == 1 ? 1u : 0u;
         *ranges = true;
       }
       k_radix_hist<kPerWaveSmall><<<grid, kSortThreads, 0, s>>>(a);
