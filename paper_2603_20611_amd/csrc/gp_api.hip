@@ -606,6 +606,7 @@ gp_status gp_render_slices_posed(gp_workspace* w, const gp_gaussians* g, const g
   if ((st = stage_batch(ws, &grp, 1, hs, ns, out, nullptr, &plan, poses)) != GP_OK) return st;
   if ((st = upload_batch(ws, plan, s)) != GP_OK) return st;
   LaunchDims d{plan.total_gauss, plan.nbins, emit_width_for(ns)};
+  d.emit_min = 64 / d.emit_width;
   d.posed = poses ? 1 : 0;
   d.one_sigma = plan.one_sigma;
   if ((st = enqueue_forward(ws, make_render_const(o, g->attr_dtype, ws), d, s)) != GP_OK) return st;

@@ -112,6 +112,7 @@ struct LaunchDims {
   int64_t gauss;        // flattened Gaussians to cover (multiple of 64)
   int64_t bins;         // bins to cover (also fixes the sort's key width)
   int32_t emit_width = 1;   // 1, 2, 4, 8 or 16: a bound (16: none) on the slices of a group
+  int32_t emit_min = 1;     // list entries that a wavefront of the emit takes at least
   int32_t posed = 0;        // the slices carry camera poses
   int32_t one_sigma = 0;    // the slices of each group are known to share one sigma_z
   // the most bins of one group (0: `bins`).  The emit writes a batch's list

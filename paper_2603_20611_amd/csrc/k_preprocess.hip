@@ -100,6 +100,7 @@ struct PreArgs {
   uint32_t sentinel_bin;
   const float* poses;   // [n_slices][12] of a posed batch
   int emit_chunk;       // Gaussians per workgroup round of the emit
+  int emit_min;         // list entries that a wavefront of the emit takes at least
   int scanned;          // wave_cnt already holds the scan (else the emit forms its bases and the totals)
   uint2* chunk_cnt;     // unscanned: the counts of 512-Gaussian chunks (compacting count), or null
   int count_lg;         // log2 of the lanes per near Gaussian in the compacting count
@@ -1119,9 +1120,12 @@ __global__ __launch_bounds__(256) void k_pre_emit(PreArgs a) {
     for (int t0 = base + wave * 64; t0 < min(base + chunk, total); t0 += 256)
       slots_wave(a, t0, form ? wave_base(bb, s_wc, (t0 - cbase) >> 6) : a.wave_cnt[t0 >> 6], list, &n_list);
     __syncthreads();
-    // the list spread over the four wavefronts
+    // the list spread over the four wavefronts, but none with less than a round of pairs:
+    // the records' arithmetic costs a wavefront the same for one lane as for 64, and on one
+    // slice four wavefronts of four Gaussians each took longer than one of sixteen
+    // (5 million Gaussians 91 -> 74 us, 100,000 14.0 -> 10.6; on eight slices no difference)
     const uint32_t n = (uint32_t)n_list;
-    const uint32_t q = min((n + 3u) / 4u, 64u);
+    const uint32_t q = min(max((n + 3u) / 4u, (uint32_t)a.emit_min), 64u);
     for (uint32_t j0 = (uint32_t)wave * q; j0 < n; j0 += 4u * q)
       emit_wave<DT, MODE>(a, n_groups, list, j0, min(q, n - j0), lds[wave]);
     __syncthreads();   // list and n_list are rewritten by the next chunk
@@ -1181,7 +1185,7 @@ hipError_t launch_reset(const Workspace& ws, bool clear_overflow, const LaunchDi
 static PreArgs pre_args(const RenderConst& rc, const Workspace& ws, uint32_t sentinel_bin) {
   return PreArgs{rc, ws.d_hdr, ws.d_groups, ws.d_slices, ws.d_ctr, ws.d_rec_pay, ws.d_rec_meta, ws.d_g_rbase,
                  ws.d_g_nrec, ws.d_g_ninst, ws.d_g_krange, ws.d_wave_cnt, ws.d_inst_key, ws.d_inst_val,
-                 sentinel_bin, ws.d_poses, 256, 1, nullptr, 0, ws.d_bin_lo, ws.d_bin_hi, 0};
+                 sentinel_bin, ws.d_poses, 256, 1, 1, nullptr, 0, ws.d_bin_lo, ws.d_bin_hi, 0};
 }
 
 hipError_t launch_pre_count(const RenderConst& rc, const Workspace& ws, const LaunchDims& d, bool clear_overflow,
@@ -1222,6 +1226,7 @@ hipError_t launch_pre_emit(const RenderConst& rc, const Workspace& ws, const Lau
   const int64_t groups = d.emit_width >= 16 ? 1024 : 512;
   a.emit_chunk = kEmitChunk;
   while (a.emit_chunk > 64 && d.gauss < groups * a.emit_chunk) a.emit_chunk /= 2;
+  a.emit_min = d.emit_min;
   int64_t blocks = (d.gauss + a.emit_chunk - 1) / a.emit_chunk;
   if (blocks > 16384) blocks = 16384;
   if (d.posed) return launch_emit_m<kEmitPosed>(a, rc.attr_dtype, (unsigned)blocks, s);
