@@ -362,7 +362,9 @@ struct BwdArgs {
 // bins): 0.582 ms with looping workgroups and rows that met in the same banks,
 // 0.450 with four wavefronts per tile, 0.365 with one; 12,288 bins of 512^2 0.070
 // against 0.064; 8,192 0.048 either way where lists are short, 0.303 against 0.333
-// where they are long; 2,048 0.042 against 0.066.  Quadrants of 8 x 8 pixels hold
+// where they are long; 2,048 0.042 against 0.066.  (Above the limit too, four are up to 8 %
+// faster where every list is long: 400,000 Gaussians on 48 slices of 256^2 1.06 against
+// 1.13; but sparse batches of that size take twice as long, 0.326 against 0.138.)  Quadrants of 8 x 8 pixels hold
 // eight offsets instead of sixteen (72 registers for 94, 0.405 against 0.450 ms)
 // but add up the moments in another order, and where filaments make the chain
 // rule cancel the gradients moved by up to 3e-4 of an element.

@@ -46,8 +46,10 @@ constexpr int kColItems = kRW * (kSH / kCol);
 // which fills 252 of the 256 threads with one batch of 18 loads (three batches of 14
 // by 168 threads, one per map: 0.237 ms for 0.178, 16 slices of 1024^2).  Maps larger
 // than the last-level cache (256 MB) come from HBM, and there whole columns of the tile
-// by half the threads, fewer loads in all, are faster still (0.157); at 200 MB both
-// take the same, at 12 MB 0.0082 against 0.0085.
+// by half the threads, fewer loads in all, are faster still (0.157).  The whole loss on
+// slices of 1024^2, by eight rows and by whole columns: 4 (100 MB) 117 and 118 us, 6 158
+// and 160, 8 (201 MB) 210 and 205, 9 245 and 235, 11 (277 MB) 293 and 278, 20 510 and
+// 486; 12 MB 0.0082 and 0.0085 for the kernel.
 constexpr int64_t kTallMinBytes = 1ll << 28;
 static_assert(kColItems <= kThreads && 3 * kRW * (kSH / 8) <= kThreads && (kSW / kRow) * kSH == kThreads, "each pass is one round of the workgroup");
 // Place of column c in a row of column sums: the even columns, then the odd ones,
